@@ -73,9 +73,7 @@ int do_assign(const ep_problem &p, const void *X, const float *C, const KmeansWs
     if (small_path_supported(p)) return launch_small_assign(p, X, C, w, labels, min_d2, objective, s);
     if (small_sliced_supported(p)) return launch_small_assign_sliced(p, X, C, w, labels, min_d2, objective, s);
     if (large_path_supported(p)) return launch_large_assign(p, X, C, w, labels, min_d2, objective, s);
-    int rc = launch_prep_centroids(p, C, w, s);
-    if (rc != EP_OK) return rc;
-    return launch_assign_generic(p, X, C, w, labels, min_d2, objective, s);
+    return launch_wide_assign(p, X, C, w, labels, min_d2, objective, s);
 }
 
 int do_update(const ep_problem &p, const void *X, const int32_t *labels, const float *C_prev, float *C_out,
@@ -83,7 +81,7 @@ int do_update(const ep_problem &p, const void *X, const int32_t *labels, const f
     const UpdateAcc acc{w.acc_sum, w.acc_cnt, w.chunk_cnt, flags};
     int rc = small_path_supported(p)    ? launch_small_update(p, X, labels, C_prev, C_out, counts, w, acc, s)
              : update_by_sorted_rows(p) ? launch_update_sorted(p, X, labels, C_prev, C_out, counts, w, acc, s)
-                                        : launch_update_small(p, X, labels, C_prev, C_out, counts, w, acc, s);
+                                        : launch_wide_update(p, X, labels, C_prev, C_out, counts, w, acc, s);
     if (rc != EP_OK || (flags & EP_UPDATE_FINALIZE)) return rc;
     return launch_accumulate_counts(p.k, acc, s);   // the running counts take this chunk's
 }
@@ -383,11 +381,12 @@ int kmeans_run_noalloc(const ep_problem *p, const void *X, int32_t iters, float 
     if (!C || !labels || !aligned(labels, 16) || !counts || iters < 0 || (flags & ~EP_RUN_FINAL_REASSIGN))
         return EP_EINVAL;
     // the problem must fit the static array: nothing is allocated to make room
-    if (carve_kmeans_ws(*p, nullptr).bytes > (size_t)EP_NOALLOC_SCRATCH_BYTES) return EP_EWORKSPACE;
+    const bool over = carve_kmeans_ws(*p, nullptr).bytes > (size_t)EP_NOALLOC_SCRATCH_BYTES;   // no update here is chunked
+    if (carve_kmeans_ws(*p, nullptr, over).bytes > (size_t)EP_NOALLOC_SCRATCH_BYTES) return EP_EWORKSPACE;
     void *ws = nullptr;
     if ((rc = scratch_of_current_device(&ws)) != EP_OK) return rc;
     // no part of the workspace has to start at zero: every kernel of a round writes what the next reads
-    return run_rounds(*p, X, iters, C, labels, counts, objective_hist, flags, carve_kmeans_ws(*p, ws),
+    return run_rounds(*p, X, iters, C, labels, counts, objective_hist, flags, carve_kmeans_ws(*p, ws, over),
                       static_cast<hipStream_t>(stream));
 }
 

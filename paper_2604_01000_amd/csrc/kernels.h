@@ -5,18 +5,16 @@
 
 namespace ep {
 
-// ---- K-Means, shape-generic kernels (kmeans_generic.hip) ----------------------
+// ---- K-Means, shared kernels (kmeans_generic.hip) ----------------------
 constexpr int kObjBlocksMax = 2048;   // partial objectives per assignment launch
-constexpr int kUpdBlocksMax = 1024;   // partial sums per small-k update launch
-constexpr int kSmallKElems = 8192;    // k*d at or below this: per-workgroup LDS partial sums
+constexpr int kUpdBlocksMax = 1024;   // partial sums per launch of the fused kernels
 constexpr int kSegWavesTarget = 16384; // sorted update: waves to spread k segments over when k is small
+constexpr int kSegRowsMin = 24;        // ... but no more than give a wave this many rows on average
+constexpr int64_t kWidePartialElems = 8 * 1024 * 1024;   // partial sums of the wide kernels (kmeans_wide.hip)
 
-// Which centroid update a problem outside the fused small-k kernels takes: per-workgroup partial sums
-// for small k * d, otherwise (and for k > 64 at d = 64 or 128, where it is several times faster)
-// rows sorted by label + segment means.  The workspace is carved accordingly.
-inline bool update_by_sorted_rows(const ep_problem &p) {
-    return (int64_t)p.k * p.d > kSmallKElems || (p.k > 64 && (p.d == 64 || p.d == 128));
-}
+// Which centroid update a problem takes: one-hot products on the matrix cores up to 64 clusters, beyond that rows
+// sorted by label + segment means.  The workspace is carved accordingly.
+inline bool update_by_sorted_rows(const ep_problem &p) { return p.k > 64; }
 
 // Chunked centroid update (the flags of kmeans_update): running sums and counts kept in the workspace
 // between the calls of one update, at a place that depends on k and d only.
@@ -65,39 +63,48 @@ struct KmeansWs {
     double *acc_sum;      // [k*d]  running sums of a chunked update
     int64_t *acc_cnt;     // [k]    running counts of a chunked update
     int64_t *chunk_cnt;   // [k]    counts of the chunk in hand
-    float *cnorm;         // [k]   generic path: ||c_j||^2; bf16 matrix-core path: -||c_j||^2 / 2 (of the rounded centroids)
-    float *cq;            // [k*d] bf16-rounded centroids as fp32 (EP_BF16 only, else unused)
-    bf16_t *cq16;         // [k*d] the same as bf16 (EP_BF16 only)
-    float *psum;          // [kUpdBlocksMax * k * d]   (small k)
-    int32_t *pcnt;        // [kUpdBlocksMax * k]       (small k)
+    float *cnorm;         // [k]   reordering-scale kernel: -||c_j||^2 / 2 of the rounded centroids
+    bf16_t *cq16;         // [k*d] reordering-scale kernel: centroids rounded to bf16
+    float *psum;          // partial sums (k <= 64)
+    int32_t *pcnt;        // partial counts (k <= 64)
+    unsigned char *wide_records;  // wide kernels: centroids as matrix-instruction operands (shares its place with what the update uses)
+    float *wide_bias;     // wide kernels: -||c_j||^2 / 2
     int64_t *idx;         // [k] init row indices
     float *best_score;    // [n] best score over the centroid slices seen so far (fp32, d in {64,128}, k > 64)
     int32_t *order;       // [n]  rows sorted by label           (large k)
     int32_t *order_tmp;   // [n]
     int64_t *seg;         // [k+1] segment offsets               (large k)
-    double *seg_part;     // [kSegWavesTarget * d] sums of the parts of long segments (large k, d = 64 or 128)
+    int seg_pieces;       // parts a segment is cut into             (k > 64)
+    double *seg_part;     // their sums, if there is more than one
     int32_t *sort_hist;   // radix-sort block histograms
     unsigned char *records;  // centroid tile records of the large-k matrix-core path
     int32_t *best_tile;   // [n] code of the 4 candidate centroid rows per point (large-k path)
     size_t bytes;
 };
-KmeansWs carve_kmeans_ws(const ep_problem &p, void *ws);
+// records_over_sums: the wide kernels' records lie over the running sums, for callers that never chunk an update.
+KmeansWs carve_kmeans_ws(const ep_problem &p, void *ws, bool records_over_sums = false);
 
 int launch_gather_rows(const ep_problem &p, const void *X, const int64_t *idx_dev, float *C, hipStream_t s);
 // S[i,:] = X[rows_dev[i],:] for i < m, element type of X, row stride ld_s.
 int launch_sample_rows(const ep_problem &p, const void *X, int64_t m, int64_t ld_s, const int64_t *rows_dev, void *S,
                        hipStream_t s);
-int launch_prep_centroids(const ep_problem &p, const float *C, const KmeansWs &w, hipStream_t s);
-int launch_assign_generic(const ep_problem &p, const void *X, const float *C, const KmeansWs &w, int32_t *labels,
-                          float *min_d2, double *objective, hipStream_t s);
-int launch_update_small(const ep_problem &p, const void *X, const int32_t *labels, const float *C_prev,
-                        float *C_out, int64_t *counts, const KmeansWs &w, const UpdateAcc &acc, hipStream_t s);
 int launch_update_sorted(const ep_problem &p, const void *X, const int32_t *labels, const float *C_prev,
                          float *C_out, int64_t *counts, const KmeansWs &w, const UpdateAcc &acc, hipStream_t s);
 // After an update call that does not finalize: cnt[j] = (accumulate ? cnt[j] : 0) + chunk_cnt[j].
 int launch_accumulate_counts(int32_t k, const UpdateAcc &acc, hipStream_t s);
 // result[0] = number of labels outside [0, k), result[1] = index of the first one (n if none).
 int launch_validate_labels(int64_t n, int32_t k, const int32_t *labels, int64_t *result, hipStream_t s);
+
+// ---- K-Means, any width (kmeans_wide.hip) ------------------------------------------------------------
+size_t wide_record_bytes(const ep_problem &p);
+size_t wide_bias_elems(const ep_problem &p);
+size_t wide_psum_elems(const ep_problem &p);
+size_t wide_pcnt_elems(const ep_problem &p);
+int launch_wide_assign(const ep_problem &p, const void *X, const float *C, const KmeansWs &w, int32_t *labels,
+                       float *min_d2, double *objective, hipStream_t s);
+// k <= 64
+int launch_wide_update(const ep_problem &p, const void *X, const int32_t *labels, const float *C_prev, float *C_out,
+                       int64_t *counts, const KmeansWs &w, const UpdateAcc &acc, hipStream_t s);
 
 // ---- K-Means, k <= 64, d in {64,128}, fp32: fused matrix-core kernels (kmeans_small.hip) --------
 constexpr int kSmallMaxBlocks = 512;  // workgroups (= partial sums) per launch; <= kUpdBlocksMax

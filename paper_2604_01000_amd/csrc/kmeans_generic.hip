@@ -1,11 +1,8 @@
-// Shape-generic K-Means kernels: any d, any k, fp32 or bf16 embeddings.  They are the
-// reference-shaped fallbacks of the library; the shapes the benchmark runs have tuned
-// kernels elsewhere and share these kernels' reductions and second passes.
+// K-Means kernels that every path shares: the initial rows, the sample, the label check, the layout of the
+// workspace, and the centroid update by sorted rows for k > 64.
 //
-// What they compute (EmbedPart paper, Alg. 3, step P <- KMeans(E, k)): one Lloyd round =
-// assign every embedding to its nearest centroid (squared Euclidean, evaluated as
-// ||c||^2 - 2 x.c, lowest index on ties), then move every centroid to the mean of its
-// embeddings (an empty cluster keeps its centroid).
+// What they compute (EmbedPart paper, Alg. 3, step P <- KMeans(E, k)): a centroid moves to the mean of the
+// embeddings assigned to it; an empty cluster keeps its centroid.
 #include <algorithm>
 #include <type_traits>
 
@@ -38,190 +35,7 @@ __global__ void sample_rows_kernel(int32_t d, int64_t m, int64_t ld, int64_t ld_
     S[t] = c < d ? X[rows[i] * ld + c] : XT(0);
 }
 
-// ---- centroid preparation: squared norms (and bf16-rounded copies) -------------------------
-// One wave per centroid; the norm is accumulated in fp64 and rounded once.
-__global__ __launch_bounds__(kBlock) void prep_centroids_kernel(int32_t d, int32_t k, int round_bf16,
-                                                                 const float *__restrict__ C,
-                                                                 float *__restrict__ cnorm, float *__restrict__ cq,
-                                                                 bf16_t *__restrict__ cq16) {
-    const int j = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-    if (j >= k) return;
-    const int lane = threadIdx.x & 63;
-    double acc = 0.0;
-    for (int m = lane; m < d; m += 64) {
-        float c = C[(int64_t)j * d + m];
-        if (round_bf16) {
-            const bf16_t q = f32_to_bf16_rne(c);
-            c = bf16_to_f32(q);
-            cq[(int64_t)j * d + m] = c;
-            cq16[(int64_t)j * d + m] = q;
-        }
-        acc += (double)c * (double)c;
-    }
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
-    if (lane == 0) cnorm[j] = (float)acc;
-}
-
-// ---- assignment ------------------------------------------------------------------------------
-// One point per lane.  Centroids pass through LDS in chunks of kChunk; each lane keeps kChunk
-// running dot products and folds them into its best (score, index) pair with a strict <, so
-// the lowest index wins ties.
-constexpr int kChunk = 16;
-constexpr int kChunkLdsFloats = 8192;  // 32 KB
-
-template <typename XT>
-__global__ __launch_bounds__(kBlock) void assign_generic_kernel(int64_t n, int32_t d, int32_t k, int64_t ld,
-                                                                 const XT *__restrict__ X,
-                                                                 const float *__restrict__ C,
-                                                                 const float *__restrict__ cnorm,
-                                                                 int32_t *__restrict__ labels,
-                                                                 float *__restrict__ min_d2,
-                                                                 double *__restrict__ obj_part) {
-    __shared__ float cs[kChunkLdsFloats];
-    __shared__ double red[kBlock / 64];
-    const int dseg = min(d, kChunkLdsFloats / kChunk);  // columns of a chunk held in LDS at once
-    double obj = 0.0;
-    const int64_t stride = (int64_t)gridDim.x * kBlock;
-    const int64_t rounds = (n + stride - 1) / stride;
-    for (int64_t it = 0; it < rounds; ++it) {
-        const int64_t i = it * stride + (int64_t)blockIdx.x * kBlock + threadIdx.x;
-        const bool valid = i < n;
-        const XT *x = X + (valid ? i : 0) * ld;
-        float best = 3.0e38f;
-        int32_t best_j = 0;
-        float xnorm = 0.f;
-        for (int32_t j0 = 0; j0 < k; j0 += kChunk) {
-            const int kc = min(kChunk, k - j0);
-            float acc[kChunk];
-#pragma unroll
-            for (int j = 0; j < kChunk; ++j) acc[j] = 0.f;
-            for (int32_t m0 = 0; m0 < d; m0 += dseg) {
-                const int dm = min(dseg, d - m0);
-                __syncthreads();
-                for (int t = threadIdx.x; t < kc * dm; t += kBlock) {
-                    const int j = t / dm, m = t % dm;
-                    cs[j * dseg + m] = C[(int64_t)(j0 + j) * d + m0 + m];
-                }
-                for (int t = threadIdx.x + kc * dseg; t < kChunk * dseg; t += kBlock) cs[t] = 0.f;  // unused slots
-                __syncthreads();
-                if (valid) {
-                    const int dm4 = dm & ~3;
-                    for (int m = 0; m < dm4; m += 4) {
-                        const float4 xv = load4(x + m0 + m);
-                        if (j0 == 0) xnorm += xv.x * xv.x + xv.y * xv.y + xv.z * xv.z + xv.w * xv.w;
-#pragma unroll
-                        for (int j = 0; j < kChunk; ++j) {
-                            const float *c = cs + j * dseg + m;
-                            acc[j] += xv.x * c[0] + xv.y * c[1] + xv.z * c[2] + xv.w * c[3];
-                        }
-                    }
-                    for (int m = dm4; m < dm; ++m) {
-                        const float xv = load_elem(x + m0 + m);
-                        if (j0 == 0) xnorm += xv * xv;
-#pragma unroll
-                        for (int j = 0; j < kChunk; ++j) acc[j] += xv * cs[j * dseg + m];
-                    }
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < kChunk; ++j) {
-                if (j < kc) {
-                    const float score = cnorm[j0 + j] - 2.f * acc[j];
-                    if (score < best) { best = score; best_j = j0 + j; }
-                }
-            }
-        }
-        if (valid) {
-            labels[i] = best_j;
-            const float d2 = fmaxf(xnorm + best, 0.f);
-            if (min_d2) min_d2[i] = d2;
-            obj += (double)d2;
-        }
-    }
-    if (obj_part) {
-        for (int off = 32; off > 0; off >>= 1) obj += __shfl_down(obj, off, 64);
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = obj;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double t = 0.0;
-            for (int w = 0; w < kBlock / 64; ++w) t += red[w];
-            obj_part[blockIdx.x] = t;
-        }
-    }
-}
-
-__global__ void sum_partials_kernel(const double *__restrict__ part, int count, double *__restrict__ out) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double t = 0.0;
-        for (int b = 0; b < count; ++b) t += part[b];
-        *out = t;
-    }
-}
-
-// ---- update, small k: per-workgroup LDS partial sums + fixed-order second pass -----------------
-// Workgroup b owns rows [b*R, (b+1)*R).  Thread t owns column t % dpad of the rows with
-// (row - b*R) % rpp == t / dpad, and adds them into its own LDS copy, so no two threads ever
-// touch the same LDS word and the order of additions is fixed.
-template <typename XT>
-__global__ __launch_bounds__(kBlock) void update_partial_kernel(int64_t n, int32_t d, int32_t k, int64_t ld,
-                                                                 int64_t rows_per_block, int dpad, int rpp,
-                                                                 const XT *__restrict__ X,
-                                                                 const int32_t *__restrict__ labels,
-                                                                 float *__restrict__ psum,
-                                                                 int32_t *__restrict__ pcnt) {
-    extern __shared__ float lds[];  // rpp * k * d floats, then rpp * k ints
-    float *sums = lds;
-    int32_t *cnts = reinterpret_cast<int32_t *>(lds + (size_t)rpp * k * d);
-    const int kd = k * d;
-    for (int t = threadIdx.x; t < rpp * kd; t += kBlock) sums[t] = 0.f;
-    for (int t = threadIdx.x; t < rpp * k; t += kBlock) cnts[t] = 0;
-    __syncthreads();
-    const int sub = threadIdx.x / dpad, col0 = threadIdx.x % dpad;
-    const int64_t b = (int64_t)blockIdx.x * rows_per_block, e = min(n, b + rows_per_block);
-    if (sub < rpp) {
-        float *mine = sums + (size_t)sub * kd;
-        for (int64_t i = b + sub; i < e; i += rpp) {
-            const int32_t l = labels[i];
-            if (l < 0 || l >= k) continue;
-            for (int m = col0; m < d; m += dpad) mine[l * d + m] += load_elem(X + i * ld + m);
-            if (col0 == 0) cnts[sub * k + l] += 1;
-        }
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < kd; t += kBlock) {
-        float s = sums[t];
-        for (int r = 1; r < rpp; ++r) s += sums[(size_t)r * kd + t];
-        psum[(int64_t)blockIdx.x * kd + t] = s;
-    }
-    for (int t = threadIdx.x; t < k; t += kBlock) {
-        int32_t c = cnts[t];
-        for (int r = 1; r < rpp; ++r) c += cnts[r * k + t];
-        pcnt[(int64_t)blockIdx.x * k + t] = c;
-    }
-}
-
 }  // namespace
-
-// Second pass shared with the fused kernels: fp64 sum of the per-workgroup partials in
-// workgroup order, divide, round to fp32; empty clusters keep C_prev.
-__global__ __launch_bounds__(kBlock) void update_finalize_kernel(int32_t d, int32_t k, int blocks,
-                                                                  const float *__restrict__ psum,
-                                                                  const int32_t *__restrict__ pcnt,
-                                                                  const float *__restrict__ C_prev,
-                                                                  float *__restrict__ C_out,
-                                                                  int64_t *__restrict__ counts, UpdateAcc acc) {
-    const int t = blockIdx.x * kBlock + threadIdx.x;
-    const int kd = k * d;
-    if (t >= kd) return;
-    const int j = t / d;
-    double s = 0.0;
-    int64_t c = 0;
-    for (int b = 0; b < blocks; ++b) {
-        s += (double)psum[(int64_t)b * kd + t];
-        c += pcnt[(int64_t)b * k + j];
-    }
-    finish_centroid_element(acc, t, j, t % d == 0, s, c, C_prev, C_out, counts);
-}
 
 __global__ void accumulate_counts_kernel(int32_t k, UpdateAcc acc) {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
@@ -282,23 +96,26 @@ __global__ void segment_offsets_kernel(int64_t n, int32_t k, const int32_t *__re
     for (int32_t j = prev + 1; j <= cur; ++j) seg[j] = i;
 }
 
-// One wave per cluster.  kLanes = d / 8 lanes share a row (8 consecutive columns each, one or two
-// 16-byte loads), so a wave reads 64 / kLanes rows per step; sums are fp64 from the start.  The row
-// groups are added in a fixed order at the end.  kLanes == 0 selects a shape-generic variant.
+// kLanes lanes share a row's slab of 8 kLanes columns (8 consecutive columns each, one or two 16-byte loads; 64
+// columns for d <= 64, else 128), so a wave reads 64 / kLanes rows per step; wider rows take several slabs, the waves
+// of one cluster's slabs side by side.  Sums are fp64 from the start.  The row groups are added in a fixed order
+// at the end.
+// load8: 8 elements at p; `second` is where the upper four of a fp32 piece lie (a piece that ends past the last
+// column repeats its lower half: those sums are not used).
 template <typename XT>
-__device__ __forceinline__ void load8(const XT *p, float (&v)[8]);
+__device__ __forceinline__ void load8(const XT *p, int second, float (&v)[8]);
 template <>
-__device__ __forceinline__ void load8<float>(const float *p, float (&v)[8]) {
-    const float4 a = *reinterpret_cast<const float4 *>(p), b = *reinterpret_cast<const float4 *>(p + 4);
+__device__ __forceinline__ void load8<float>(const float *p, int second, float (&v)[8]) {
+    const float4 a = *reinterpret_cast<const float4 *>(p), b = *reinterpret_cast<const float4 *>(p + second);
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
 template <>
-__device__ __forceinline__ void load8<f16_t>(const f16_t *p, float (&v)[8]) {
+__device__ __forceinline__ void load8<f16_t>(const f16_t *p, int, float (&v)[8]) {
     const float4 a = load4(p), b = load4(p + 4);
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
 template <>
-__device__ __forceinline__ void load8<bf16_t>(const bf16_t *p, float (&v)[8]) {
+__device__ __forceinline__ void load8<bf16_t>(const bf16_t *p, int, float (&v)[8]) {
     const uint4 r = *reinterpret_cast<const uint4 *>(p);
     v[0] = __uint_as_float(r.x << 16); v[1] = __uint_as_float(r.x & 0xFFFF0000u);
     v[2] = __uint_as_float(r.y << 16); v[3] = __uint_as_float(r.y & 0xFFFF0000u);
@@ -306,14 +123,18 @@ __device__ __forceinline__ void load8<bf16_t>(const bf16_t *p, float (&v)[8]) {
     v[6] = __uint_as_float(r.w << 16); v[7] = __uint_as_float(r.w & 0xFFFF0000u);
 }
 
-// Sum of the rows order[b .. e) in fp64 by one wave, for d = 8 * kLanes: lane = (sub, chunk) adds the
-// rows b + sub, b + sub + 64 / kLanes, ... in 8 columns, then the sub-lanes are added in a fixed
-// butterfly.  Every lane ends with the totals of its 8 columns.
+// Sum of the rows order[b .. e) over one slab in fp64 by one wave: lane = (sub, chunk) adds the rows b + sub,
+// b + sub + 64 / kLanes, ... in 8 columns, then the sub-lanes are added in a fixed butterfly.  Every lane ends with
+// the totals of its 8 columns.
 template <typename XT, int kLanes>
-__device__ __forceinline__ void sum_sorted_rows(const XT *__restrict__ X, int64_t ld, const int32_t *__restrict__ order,
-                                                int64_t b, int64_t e, int lane, double (&acc)[8]) {
-    constexpr int kL = kLanes > 0 ? kLanes : 1, kRows = 64 / kL;
-    const int chunk = lane % kL, sub = lane / kL;
+__device__ __forceinline__ void sum_sorted_rows(const XT *__restrict__ X, int64_t ld, int32_t d, int slab,
+                                                const int32_t *__restrict__ order, int64_t b, int64_t e, int lane,
+                                                double (&acc)[8]) {
+    constexpr int kRows = 64 / kLanes;
+    const int chunk = lane % kLanes, sub = lane / kLanes;
+    const int col = slab * 8 * kLanes + 8 * chunk;
+    const XT *Xc = X + (col < d ? col : 0);          // a lane without columns reads column 0
+    const int second = col + 4 < d ? 4 : 0;
 #pragma unroll
     for (int q = 0; q < 8; ++q) acc[q] = 0.0;
     // Four rows in flight per lane, and the row indices of the next four loaded (unconditionally, from positions
@@ -332,7 +153,7 @@ __device__ __forceinline__ void sum_sorted_rows(const XT *__restrict__ X, int64_
             for (int r = 0; r < kAhead; ++r) nx[r] = index_at(t + (kAhead + r) * kRows);
             float v[kAhead][8];
 #pragma unroll
-            for (int r = 0; r < kAhead; ++r) load8(X + a[r] * ld + 8 * chunk, v[r]);
+            for (int r = 0; r < kAhead; ++r) load8(Xc + a[r] * ld, second, v[r]);
 #pragma unroll
             for (int r = 0; r < kAhead; ++r)
 #pragma unroll
@@ -344,40 +165,42 @@ __device__ __forceinline__ void sum_sorted_rows(const XT *__restrict__ X, int64_
         for (int r = 0; r < kAhead - 1; ++r) {   // what is left of this lane's rows, one by one (their indices are loaded)
             if (t + r * kRows < e) {
                 float v0[8];
-                load8(X + a[r] * ld + 8 * chunk, v0);
+                load8(Xc + a[r] * ld, second, v0);
 #pragma unroll
                 for (int q = 0; q < 8; ++q) acc[q] += (double)v0[q];
             }
         }
     }
 #pragma unroll
-    for (int off = kL; off < 64; off <<= 1)
+    for (int off = kLanes; off < 64; off <<= 1)
 #pragma unroll
         for (int q = 0; q < 8; ++q) acc[q] += __shfl_xor(acc[q], off, 64);
 }
 
 // Few, long segments (k well below the number of waves the chip runs): every segment is cut into
-// `pieces` contiguous parts, one wave each; the parts' sums go to the workspace in fp64 and
-// segment_combine_kernel adds them in order.  The cut depends on (n, k) only: reproducible.
+// `pieces` contiguous parts, one wave each and slab; the parts' sums go to the workspace in fp64 and
+// segment_combine_kernel adds them in order.  The cut depends on (n, k, d) only: reproducible.
 template <typename XT, int kLanes>
-__global__ __launch_bounds__(kBlock) void segment_partial_kernel(int32_t d, int32_t k, int32_t pieces, int64_t ld,
-                                                                  const XT *__restrict__ X,
+__global__ __launch_bounds__(kBlock) void segment_partial_kernel(int32_t d, int32_t k, int32_t slabs, int32_t pieces,
+                                                                  int64_t ld, const XT *__restrict__ X,
                                                                   const int32_t *__restrict__ order,
                                                                   const int64_t *__restrict__ seg,
                                                                   double *__restrict__ part) {
     const int64_t w = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-    if (w >= (int64_t)k * pieces) return;
-    const int j = (int)(w / pieces), piece = (int)(w % pieces), lane = threadIdx.x & 63;
+    if (w >= (int64_t)k * pieces * slabs) return;
+    const int slab = (int)(w % slabs), lane = threadIdx.x & 63;
+    const int64_t wp = w / slabs;
+    const int j = (int)(wp / pieces), piece = (int)(wp % pieces);
     const int64_t b = seg[j], cnt = seg[j + 1] - b;
     double acc[8];
-    sum_sorted_rows<XT, kLanes>(X, ld, order, b + cnt * piece / pieces, b + cnt * (piece + 1) / pieces, lane, acc);
+    sum_sorted_rows<XT, kLanes>(X, ld, d, slab, order, b + cnt * piece / pieces, b + cnt * (piece + 1) / pieces, lane, acc);
     if (lane < kLanes) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q) part[w * d + 8 * lane + q] = acc[q];
+        for (int q = 0; q < 8; ++q) part[w * 8 * kLanes + 8 * lane + q] = acc[q];
     }
 }
 
-__global__ __launch_bounds__(kBlock) void segment_combine_kernel(int32_t d, int32_t k, int32_t pieces,
+__global__ __launch_bounds__(kBlock) void segment_combine_kernel(int32_t d, int32_t k, int32_t dseg, int32_t pieces,
                                                                   const int64_t *__restrict__ seg,
                                                                   const double *__restrict__ part,
                                                                   const float *__restrict__ C_prev,
@@ -388,47 +211,32 @@ __global__ __launch_bounds__(kBlock) void segment_combine_kernel(int32_t d, int3
     const int j = (int)(t / d), col = (int)(t % d);
     const int64_t cnt = seg[j + 1] - seg[j];
     double tot = 0.0;
-    for (int piece = 0; piece < pieces; ++piece) tot += part[((int64_t)j * pieces + piece) * d + col];
+    for (int piece = 0; piece < pieces; ++piece) tot += part[((int64_t)j * pieces + piece) * dseg + col];
     finish_centroid_element(acc, t, j, col == 0, tot, cnt, C_prev, C_out, counts);
 }
 
 template <typename XT, int kLanes>
-__global__ __launch_bounds__(kBlock) void segment_mean_kernel(int32_t d, int32_t k, int64_t ld,
+__global__ __launch_bounds__(kBlock) void segment_mean_kernel(int32_t d, int32_t k, int32_t slabs, int64_t ld,
                                                                const XT *__restrict__ X,
                                                                const int32_t *__restrict__ order,
                                                                const int64_t *__restrict__ seg,
                                                                const float *__restrict__ C_prev,
                                                                float *__restrict__ C_out,
                                                                int64_t *__restrict__ counts, UpdateAcc upd) {
-    const int j = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-    if (j >= k) return;
-    const int lane = threadIdx.x & 63;
+    const int64_t w = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    if (w >= (int64_t)k * slabs) return;
+    const int j = (int)(w / slabs), slab = (int)(w % slabs), lane = threadIdx.x & 63;
     const int64_t b = seg[j], e = seg[j + 1];
     const int64_t cnt = e - b;
-    if (kLanes > 0) {
-        const int chunk = lane % (kLanes > 0 ? kLanes : 1), sub = lane / (kLanes > 0 ? kLanes : 1);
-        double acc[8];
-        sum_sorted_rows<XT, kLanes>(X, ld, order, b, e, lane, acc);
-        if (sub == 0) {
+    const int chunk = lane % kLanes, sub = lane / kLanes;
+    double acc[8];
+    sum_sorted_rows<XT, kLanes>(X, ld, d, slab, order, b, e, lane, acc);
+    if (sub == 0) {
+        const int col = slab * 8 * kLanes + 8 * chunk;
 #pragma unroll
-            for (int q = 0; q < 8; ++q)
-                finish_centroid_element(upd, (int64_t)j * d + 8 * chunk + q, j, chunk == 0 && q == 0, acc[q], cnt, C_prev,
-                                        C_out, counts);
-        }
-        return;
-    }
-    for (int m0 = 0; m0 < d; m0 += 128) {  // shape-generic: two columns per lane per sweep
-        const int m = m0 + 2 * lane;
-        double s0 = 0.0, s1 = 0.0;
-        if (m < d) {
-            for (int64_t t = b; t < e; ++t) {
-                const XT *x = X + (int64_t)order[t] * ld + m;
-                s0 += (double)load_elem(x);
-                if (m + 1 < d) s1 += (double)load_elem(x + 1);
-            }
-            finish_centroid_element(upd, (int64_t)j * d + m, j, m == 0, s0, cnt, C_prev, C_out, counts);
-            if (m + 1 < d) finish_centroid_element(upd, (int64_t)j * d + m + 1, j, false, s1, cnt, C_prev, C_out, counts);
-        }
+        for (int q = 0; q < 8; ++q)
+            if (col + q < d)
+                finish_centroid_element(upd, (int64_t)j * d + col + q, j, col + q == 0, acc[q], cnt, C_prev, C_out, counts);
     }
 }
 
@@ -441,37 +249,73 @@ int by_dtype(const ep_problem &p, F &&f) {
 
 }  // namespace
 
-KmeansWs carve_kmeans_ws(const ep_problem &p, void *ws) {
+namespace {
+// Slabs of the sorted update, and the parts a segment is cut into: enough waves to fill the chip, at least a few
+// rows each, and (at widths other than 64 and 128, where the rest of the workspace fits the static array of
+// kmeans_run_noalloc) no more than that array has room for.
+struct SegPlan {
+    int lanes, slabs, pieces;
+    size_t part_elems() const { return (size_t)slabs * 8 * lanes; }   // per cluster and piece
+};
+SegPlan seg_plan(const ep_problem &p, size_t other_bytes) {
+    SegPlan s;
+    s.lanes = p.d <= 64 ? 8 : 16;
+    s.slabs = (int)ceil_div(p.d, 8 * s.lanes);
+    int64_t pieces = std::min<int64_t>(kSegWavesTarget / ((int64_t)p.k * s.slabs), p.n / ((int64_t)p.k * kSegRowsMin));
+    if (p.d != 64 && p.d != 128 && other_bytes < (size_t)EP_NOALLOC_SCRATCH_BYTES)
+        pieces = std::min<int64_t>(pieces, ((size_t)EP_NOALLOC_SCRATCH_BYTES - other_bytes) / ((size_t)p.k * s.part_elems() * 8));
+    s.pieces = (int)std::max<int64_t>(1, pieces);
+    return s;
+}
+}  // namespace
+
+KmeansWs carve_kmeans_ws(const ep_problem &p, void *ws, bool records_over_sums) {
     Carver c(ws);
     KmeansWs w{};
     const size_t kd = (size_t)p.k * p.d;
+    const bool small = small_path_supported(p), large = large_path_supported(p);
+    const bool wide = !small && !large && !small_sliced_supported(p);
+    const size_t rec_bytes = wide ? wide_record_bytes(p) : 0;
     w.obj_part = c.take<double>(kObjBlocksMax);
     // the running sums of a chunked update come first: their place must not depend on n, because the
     // chunks of one update may differ in size
-    w.acc_sum = c.take<double>(kd);
+    w.acc_sum = reinterpret_cast<double *>(c.take<unsigned char>(std::max(kd * 8, records_over_sums ? rec_bytes : 0)));
     w.acc_cnt = c.take<int64_t>(p.k);
     w.chunk_cnt = c.take<int64_t>(p.k);
-    w.cnorm = c.take<float>(p.k);
     w.idx = c.take<int64_t>(p.k);
-    if (p.dtype == EP_BF16) {
-        w.cq = c.take<float>(kd);
+    if (large) {
+        w.cnorm = c.take<float>(p.k);
         w.cq16 = c.take<bf16_t>(kd);
-    }
-    if (small_sliced_supported(p)) w.best_score = c.take<float>((size_t)p.n);
-    if (!update_by_sorted_rows(p)) {
-        w.psum = c.take<float>((size_t)kUpdBlocksMax * std::max(kd, (size_t)p.k * (size_t)small_padded_d(p)));
-        w.pcnt = c.take<int32_t>((size_t)kUpdBlocksMax * p.k);
-    } else {
-        w.order = c.take<int32_t>((size_t)p.n);
-        w.order_tmp = c.take<int32_t>((size_t)p.n);
-        w.seg = c.take<int64_t>((size_t)p.k + 1);
-        if (p.d == 64 || p.d == 128) w.seg_part = c.take<double>((size_t)kSegWavesTarget * p.d);
-        w.sort_hist = c.take<int32_t>(sort_hist_elems());
-    }
-    if (large_path_supported(p)) {
         w.records = c.take<unsigned char>(large_record_bytes(p));
         w.best_tile = c.take<int32_t>((size_t)p.n);
     }
+    if (wide) w.wide_bias = c.take<float>(wide_bias_elems(p));
+    if (small_sliced_supported(p)) w.best_score = c.take<float>((size_t)p.n);
+    if (small) {
+        w.psum = c.take<float>((size_t)kUpdBlocksMax * (size_t)p.k * (size_t)small_padded_d(p));
+        w.pcnt = c.take<int32_t>((size_t)kUpdBlocksMax * p.k);
+    } else if (!update_by_sorted_rows(p)) {
+        // the assignment is through with its records when the update writes its partial sums: one place for both
+        unsigned char *both = c.take<unsigned char>(std::max(wide_psum_elems(p) * 4, records_over_sums ? 0 : rec_bytes));
+        w.psum = reinterpret_cast<float *>(both);
+        w.wide_records = both;
+        w.pcnt = c.take<int32_t>(wide_pcnt_elems(p));
+    } else {
+        const size_t n4 = align_up((size_t)p.n * 4, 256);
+        unsigned char *both = c.take<unsigned char>(std::max(2 * n4, records_over_sums ? 0 : rec_bytes));
+        w.order = reinterpret_cast<int32_t *>(both);   // (the same for the row order)
+        w.order_tmp = reinterpret_cast<int32_t *>(both + n4);
+        w.wide_records = both;
+        w.seg = c.take<int64_t>((size_t)p.k + 1);
+        w.sort_hist = c.take<int32_t>(sort_hist_elems());
+        // (the parts must not depend on where the records lie: count them as lying over the sums)
+        const size_t moved = records_over_sums ? 0 : align_up(std::max(kd * 8, rec_bytes), 256) - align_up(kd * 8, 256);
+        const size_t shared = records_over_sums ? 0 : align_up(std::max(2 * n4, rec_bytes), 256) - 2 * n4;
+        const SegPlan sp = seg_plan(p, align_up(c.used, 256) + moved - shared + 256);
+        w.seg_pieces = sp.pieces;
+        if (sp.pieces > 1) w.seg_part = c.take<double>((size_t)p.k * sp.pieces * sp.part_elems());
+    }
+    if (records_over_sums) w.wide_records = reinterpret_cast<unsigned char *>(w.acc_sum);
     w.bytes = align_up(c.used, 256);
     return w;
 }
@@ -499,34 +343,6 @@ int launch_sample_rows(const ep_problem &p, const void *X, int64_t m, int64_t ld
     });
 }
 
-int launch_prep_centroids(const ep_problem &p, const float *C, const KmeansWs &w, hipStream_t s) {
-    prep_centroids_kernel<<<(unsigned)ceil_div(p.k, kBlock / 64), kBlock, 0, s>>>(
-        p.d, p.k, p.dtype == EP_BF16, C, w.cnorm, w.cq, w.cq16);
-    EP_LAUNCH_CHECK();
-    return EP_OK;
-}
-
-int launch_assign_generic(const ep_problem &p, const void *X, const float *C, const KmeansWs &w, int32_t *labels,
-                          float *min_d2, double *objective, hipStream_t s) {
-    const int blocks = (int)std::min<int64_t>(kObjBlocksMax, ceil_div(p.n, kBlock));
-    const float *Cuse = p.dtype == EP_BF16 ? w.cq : C;
-    int rc = by_dtype(p, [&](auto *tag) {
-        using XT = std::remove_cv_t<std::remove_pointer_t<decltype(tag)>>;
-        ProfScope prof(EP_PROF_LLOYD_MAIN, s);
-        assign_generic_kernel<XT><<<blocks, kBlock, 0, s>>>(p.n, p.d, p.k, p.ld, static_cast<const XT *>(X), Cuse,
-                                                            w.cnorm, labels, min_d2,
-                                                            objective ? w.obj_part : nullptr);
-        EP_LAUNCH_CHECK();
-        return EP_OK;
-    });
-    if (rc != EP_OK) return rc;
-    if (objective) {
-        sum_partials_kernel<<<1, 64, 0, s>>>(w.obj_part, blocks, objective);
-        EP_LAUNCH_CHECK();
-    }
-    return EP_OK;
-}
-
 int launch_accumulate_counts(int32_t k, const UpdateAcc &acc, hipStream_t s) {
     accumulate_counts_kernel<<<(unsigned)ceil_div(k, kBlock), kBlock, 0, s>>>(k, acc);
     EP_LAUNCH_CHECK();
@@ -543,31 +359,6 @@ int launch_validate_labels(int64_t n, int32_t k, const int32_t *labels, int64_t 
     return EP_OK;
 }
 
-int launch_update_small(const ep_problem &p, const void *X, const int32_t *labels, const float *C_prev,
-                        float *C_out, int64_t *counts, const KmeansWs &w, const UpdateAcc &acc, hipStream_t s) {
-    const int kd = p.k * p.d;
-    int dpad = 1;
-    while (dpad < p.d && dpad < kBlock) dpad <<= 1;
-    int rpp = kBlock / dpad;
-    while (rpp > 1 && (size_t)rpp * (kd + p.k) * 4 > 64 * 1024) rpp >>= 1;
-    const size_t lds = (size_t)rpp * (kd + p.k) * 4;
-    int64_t rows_per_block = std::max<int64_t>(ceil_div(p.n, kUpdBlocksMax), 64);
-    const int blocks = (int)ceil_div(p.n, rows_per_block);
-    int rc = by_dtype(p, [&](auto *tag) {
-        using XT = std::remove_cv_t<std::remove_pointer_t<decltype(tag)>>;
-        ProfScope prof(EP_PROF_UPDATE_SUMS, s);
-        update_partial_kernel<XT><<<blocks, kBlock, lds, s>>>(p.n, p.d, p.k, p.ld, rows_per_block, dpad, rpp,
-                                                              static_cast<const XT *>(X), labels, w.psum, w.pcnt);
-        EP_LAUNCH_CHECK();
-        return EP_OK;
-    });
-    if (rc != EP_OK) return rc;
-    update_finalize_kernel<<<(unsigned)ceil_div(kd, kBlock), kBlock, 0, s>>>(p.d, p.k, blocks, w.psum, w.pcnt, C_prev,
-                                                                             C_out, counts, acc);
-    EP_LAUNCH_CHECK();
-    return EP_OK;
-}
-
 int launch_update_sorted(const ep_problem &p, const void *X, const int32_t *labels, const float *C_prev,
                          float *C_out, int64_t *counts, const KmeansWs &w, const UpdateAcc &acc, hipStream_t s) {
     int rc = launch_sort_by_label(p.n, p.k, labels, nullptr, w.order, w.order_tmp, w.sort_hist, s);
@@ -577,27 +368,24 @@ int launch_update_sorted(const ep_problem &p, const void *X, const int32_t *labe
     return by_dtype(p, [&](auto *tag) {
         using XT = std::remove_cv_t<std::remove_pointer_t<decltype(tag)>>;
         ProfScope prof(EP_PROF_UPDATE_SUMS, s);
-        const unsigned grid = (unsigned)ceil_div(p.k, kBlock / 64);
         const XT *Xt = static_cast<const XT *>(X);
-        const int pieces = kSegWavesTarget / p.k;   // waves per segment; k * pieces <= kSegWavesTarget
-        if (pieces >= 2 && w.seg_part) {
-            const unsigned pgrid = (unsigned)ceil_div((int64_t)p.k * pieces, kBlock / 64);
-            if (p.d == 128)
-                segment_partial_kernel<XT, 16><<<pgrid, kBlock, 0, s>>>(p.d, p.k, pieces, p.ld, Xt, w.order, w.seg, w.seg_part);
+        const int lanes = p.d <= 64 ? 8 : 16, slabs = (int)ceil_div(p.d, 8 * lanes), pieces = w.seg_pieces;
+        const unsigned grid = (unsigned)ceil_div((int64_t)p.k * slabs * pieces, kBlock / 64);
+        if (pieces > 1) {
+            if (lanes == 16)
+                segment_partial_kernel<XT, 16><<<grid, kBlock, 0, s>>>(p.d, p.k, slabs, pieces, p.ld, Xt, w.order, w.seg, w.seg_part);
             else
-                segment_partial_kernel<XT, 8><<<pgrid, kBlock, 0, s>>>(p.d, p.k, pieces, p.ld, Xt, w.order, w.seg, w.seg_part);
+                segment_partial_kernel<XT, 8><<<grid, kBlock, 0, s>>>(p.d, p.k, slabs, pieces, p.ld, Xt, w.order, w.seg, w.seg_part);
             EP_LAUNCH_CHECK();
             segment_combine_kernel<<<(unsigned)ceil_div((int64_t)p.k * p.d, kBlock), kBlock, 0, s>>>(
-                p.d, p.k, pieces, w.seg, w.seg_part, C_prev, C_out, counts, acc);
+                p.d, p.k, slabs * 8 * lanes, pieces, w.seg, w.seg_part, C_prev, C_out, counts, acc);
             EP_LAUNCH_CHECK();
             return EP_OK;
         }
-        if (p.d == 128)
-            segment_mean_kernel<XT, 16><<<grid, kBlock, 0, s>>>(p.d, p.k, p.ld, Xt, w.order, w.seg, C_prev, C_out, counts, acc);
-        else if (p.d == 64)
-            segment_mean_kernel<XT, 8><<<grid, kBlock, 0, s>>>(p.d, p.k, p.ld, Xt, w.order, w.seg, C_prev, C_out, counts, acc);
+        if (lanes == 16)
+            segment_mean_kernel<XT, 16><<<grid, kBlock, 0, s>>>(p.d, p.k, slabs, p.ld, Xt, w.order, w.seg, C_prev, C_out, counts, acc);
         else
-            segment_mean_kernel<XT, 0><<<grid, kBlock, 0, s>>>(p.d, p.k, p.ld, Xt, w.order, w.seg, C_prev, C_out, counts, acc);
+            segment_mean_kernel<XT, 8><<<grid, kBlock, 0, s>>>(p.d, p.k, slabs, p.ld, Xt, w.order, w.seg, C_prev, C_out, counts, acc);
         EP_LAUNCH_CHECK();
         return EP_OK;
     });
