@@ -238,9 +238,8 @@ int launch_edge_gap(int64_t n, int64_t nnz, const void *rowptr, bool i64, const 
 
 // ---- balancing (balance.hip) -------------------------------------------------------
 struct BalanceWs {
-    unsigned char *plan;  // per-round plan (loads, moves, free capacities, threshold degrees)
-    uint32_t *degree_hist;   // [k * bins] class members per partition and degree
-    int32_t *tie;            // per vertex range and partition: members at the threshold degree
+    unsigned char *shared;   // barrier counters, histograms and arrivals that the workgroups of a call share
+    unsigned int *tie;       // per workgroup and partition: members at the threshold degree
     size_t bytes;
 };
 BalanceWs carve_balance_ws(int64_t n, void *ws);

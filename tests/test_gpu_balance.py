@@ -158,3 +158,38 @@ def test_cluster_and_balance_is_phase_two_of_the_method(name, sample, with_class
     sizes = np.bincount(want, minlength=w.k)
     if not with_classes:
         assert sizes.max() <= max(np.floor(beta[2] * w.n / w.k), np.ceil(w.n / w.k))
+
+
+@pytest.mark.parametrize("n,k,beta", [
+    (32_768, 9, 1.0), (32_769, 9, 1.0),      # last size of one workgroup, first of several (several rounds at beta = 1)
+    (32_769 + 2_048, 255, 1.0),              # one workgroup more, the largest k (32 degree bins)
+    (524_289, 3, 1.0),                       # first size whose ranges are longer than the shortest
+])
+def test_balance_at_the_edges_of_the_launch_shapes(n, k, beta):
+    rng = np.random.default_rng(n + k)
+    rowptr = np.concatenate([[0], np.cumsum(rng.integers(0, 12, n))]).astype(np.int64)   # ties at every threshold
+    vclass = rng.integers(0, 2, n).astype(np.uint8)
+    labels = _skewed_labels(n, k, n)
+    want, st_or = oracle.balance(rowptr, labels, k, beta, seed=7, max_rounds=40, vclass=vclass, class_id=1)
+    got, st = _device_balance(rowptr, labels, k, beta, 7, 40, vclass, 1)
+    np.testing.assert_array_equal(got, want)
+    np.testing.assert_array_equal(st, st_or)
+
+
+def test_calls_on_several_streams_do_not_disturb_each_other():
+    n, k = 120_000, 12
+    rng = np.random.default_rng(3)
+    rowptr = torch.from_numpy(np.concatenate([[0], np.cumsum(rng.integers(0, 40, n))]).astype(np.int64)).to(DEV)
+    labels = [_skewed_labels(n, k, s) for s in range(4)]
+    want = [_device_balance(rowptr, lab, k, 1.05, 5, 16)[0] for lab in labels]
+    got = [torch.from_numpy(lab).to(DEV) for lab in labels]
+    stats = [torch.zeros(3, dtype=torch.int64, device=DEV) for _ in labels]
+    ws = [ep.workspace(ep.balance_workspace_bytes(n), DEV) for _ in labels]
+    streams = [torch.cuda.Stream() for _ in labels]
+    torch.cuda.synchronize()
+    for lab, st, w, stream in zip(got, stats, ws, streams):
+        with torch.cuda.stream(stream):
+            ep.partition_balance(n, k, rowptr, None, 0, 1.05, 5, 16, lab, st, w)
+    torch.cuda.synchronize()
+    for a, b in zip(got, want):
+        np.testing.assert_array_equal(a.cpu().numpy(), b)
