@@ -94,12 +94,37 @@ __global__ __launch_bounds__(256) void wide_prep_kernel(int32_t d, int32_t k, in
 }
 
 // ---- 2. assignment ----------------------------------------------------------------------------------
+constexpr float kNoScore = -3.4e38f;   // no score was ordered above it: a row with an infinity or a NaN
+
+// The scores of a row in plain fp32, for the rows whose split has no value (the terms of an infinity are infinity
+// and NaN).  A row with an infinity takes the first centroid whose product with it is +infinity; one with a NaN keeps
+// label 0, as comparisons with NaN leave it.
+template <typename XT>
+__device__ void plain_scores(const XT *x, int32_t d, const float *C, const float *bias, int32_t k, float &best, int32_t &idx) {
+    bool nan = false;
+    for (int m = 0; m < d; ++m) {
+        const float v = load_elem(x + m);
+        nan |= v != v;
+    }
+    if (nan) return;
+    for (int32_t j = 0; j < k; ++j) {
+        float s = bias[j];
+        for (int m = 0; m < d; ++m) {
+            float c = C[(int64_t)j * d + m];
+            if (std::is_same<XT, bf16_t>::value) c = bf16_to_f32(f32_to_bf16_rne(c));
+            s = fmaf(load_elem(x + m), c, s);
+        }
+        if (s > best) { best = s; idx = j; }
+    }
+}
+
 // XN: also ||x||^2 (min_d2 or the objective is wanted).
 template <typename XT, int KT, int PT, bool XN>
 __global__ __launch_bounds__(kAssignThreads, 2) void wide_assign_kernel(
     int64_t n, int32_t d, int64_t ld, int32_t ksteps, int32_t panel_steps, int32_t blocks_of_centroids,
     const XT *__restrict__ X, const unsigned char *__restrict__ records, const float *__restrict__ bias,
-    int32_t *__restrict__ labels, float *__restrict__ min_d2, double *__restrict__ obj_part) {
+    const float *__restrict__ C, int32_t k, int32_t *__restrict__ labels, float *__restrict__ min_d2,
+    double *__restrict__ obj_part) {
     constexpr bool kF32 = std::is_same<XT, float>::value, kBf16 = std::is_same<XT, bf16_t>::value;
     constexpr int CT = kBf16 ? 1 : 3;            // terms of a centroid element
     constexpr int TX = x_terms<XT>();
@@ -257,6 +282,8 @@ __global__ __launch_bounds__(kAssignThreads, 2) void wide_assign_kernel(
             if (g == p) my_best = b, my_idx = i, my_xn = x2;
         }
         const int64_t i = tile * tile_rows + (wave * PT + g) * 16 + c;
+        if (__builtin_expect(__any(g < PT && i < n && my_best == kNoScore), 0))
+            if (g < PT && i < n && my_best == kNoScore) plain_scores(X + i * ld, d, C, bias, k, my_best, my_idx);
         if (g < PT && i < n) {
             labels[i] = my_idx;
             if (XN) {
@@ -268,7 +295,7 @@ __global__ __launch_bounds__(kAssignThreads, 2) void wide_assign_kernel(
     };
     auto begin_tile = [&]() {
 #pragma unroll
-        for (int p = 0; p < PT; ++p) best[p] = -3.4e38f, bidx[p] = 0, xn[p] = 0.f;
+        for (int p = 0; p < PT; ++p) best[p] = kNoScore, bidx[p] = 0, xn[p] = 0.f;
         cb = 0;
     };
     // One K-step is worked on while the next one (of the next tile, if need be) is in flight.
@@ -433,6 +460,39 @@ __global__ __launch_bounds__(256, 2) void wide_sums_kernel(int64_t n, int32_t d,
         add(xb, lb);
         ++grp;
     }
+    // An infinity or a NaN times the zeros of the one-hot operand is a NaN in every centroid's sum: then this part's
+    // rows are added again one by one, each to its own centroid only.  (Columns past d may hold anything.)
+    bool odd = false;
+#pragma unroll
+    for (int t = 0; t < NC; ++t)
+        if (col + t < d) {
+#pragma unroll
+            for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) odd |= !(fabsf(acc[mt][t][v]) < __builtin_inff());
+        }
+    if (__builtin_expect(__any(odd), 0)) {
+#pragma unroll
+        for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+            for (int t = 0; t < NC; ++t) acc[mt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int64_t r = first * 32; r < min(n, last * 32); ++r) {
+            const int32_t l = labels[r];
+            const u32x4 x = *reinterpret_cast<const u32x4 *>(Xc + r * ld);
+#pragma unroll
+            for (int t = 0; t < NC; ++t) {
+                float xv;
+                if constexpr (kF32) xv = __uint_as_float(x[t]);
+                else if constexpr (kBf16) xv = bf16_to_f32((bf16_t)(x[t >> 1] >> (16 * (t & 1))));
+                else xv = (float)__builtin_bit_cast(_Float16, (unsigned short)(x[t >> 1] >> (16 * (t & 1))));
+#pragma unroll
+                for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (l == 16 * mt + 4 * g + v) acc[mt][t][v] += xv;
+            }
+        }
+    }
     const int64_t dpad = (int64_t)slabs * 16 * NC;
 #pragma unroll
     for (int mt = 0; mt < KT; ++mt) {
@@ -579,7 +639,7 @@ int launch_wide_assign(const ep_problem &p, const void *X, const float *C, const
                 }
                 ProfScope prof(EP_PROF_LLOYD_MAIN, s);
                 kern.value<<<grid, threads, lds, s>>>(p.n, p.d, p.ld, ksteps, panel_steps, blocks, static_cast<const XT *>(X),
-                                                      w.wide_records, w.wide_bias, labels, min_d2,
+                                                      w.wide_records, w.wide_bias, C, p.k, labels, min_d2,
                                                       objective ? w.obj_part : nullptr);
                 EP_LAUNCH_CHECK();
                 return (int)EP_OK;

@@ -59,3 +59,35 @@ def test_wide_lockstep(n, d, k, dtype):
     C_got, counts = Kmeans(X, k).update(labels, C0.astype(np.float32))
     np.testing.assert_array_equal(counts, counts_or)
     assert centroid_rel_err(C_got, C_or) <= CENTROID_RTOL
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("n,d,k", [(3_001, 132, 20), (140_000, 70, 49)])
+def test_wide_infinities_stay_in_their_cluster(n, d, k, dtype):
+    g = torch.Generator().manual_seed(n)
+    unit = 4 if dtype == torch.float32 else 8
+    padded = torch.full((n, (d + unit - 1) // unit * unit), float("nan"), dtype=dtype)
+    padded[:, :d] = torch.randn(n, d, generator=g).to(dtype)
+    C0 = torch.randn(k, d, generator=g).to(torch.bfloat16).float().numpy()
+    clean, clean_d2, _ = Kmeans(padded.to(DEV)[:, :d], k).set_centroids(C0).assign()
+    plants = [(5, 3, float("inf")), (40, d - 1, float("-inf")), (n - 1, 0, float("nan"))]
+    for row, col, value in plants:
+        padded[row, col] = value
+    X = padded.to(DEV)[:, :d]
+    got, d2, _ = Kmeans(X, k).set_centroids(C0).assign()
+    odd = np.array([row for row, _, _ in plants])
+    rest = np.delete(np.arange(n), odd)
+    np.testing.assert_array_equal(got[rest], clean[rest])
+    np.testing.assert_array_equal(d2[rest], clean_d2[rest])
+    assert got[5] == np.nonzero(C0[:, 3] > 0)[0][0] and got[40] == np.nonzero(C0[:, d - 1] < 0)[0][0] and got[n - 1] == 0
+
+    labels = np.random.default_rng(n).integers(0, k, size=n).astype(np.int32)
+    labels[odd] = [1, 1, 2]
+    C_or, counts_or, _ = oracle.update(to_np32(X), labels, C0.astype(np.float64))
+    C_got, counts = Kmeans(X, k).update(labels, C0)
+    np.testing.assert_array_equal(counts, counts_or)
+    finite = np.isfinite(C_or)
+    assert finite.sum() == k * d - 3
+    np.testing.assert_array_equal(np.isfinite(C_got), finite)
+    assert C_got[1, 3] == np.inf and C_got[1, d - 1] == -np.inf and np.isnan(C_got[2, 0])
+    assert np.abs(C_got[finite] - C_or[finite]).max() <= CENTROID_RTOL * np.abs(C_or[finite]).max()
