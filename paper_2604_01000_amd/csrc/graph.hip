@@ -100,76 +100,17 @@ __global__ __launch_bounds__(kBlock) void label_prep_kernel(int64_t n, int32_t k
 }
 
 // ---- CSR sweeps -------------------------------------------------------------------------
-// L consecutive lanes own one row and stride over its entries, so rows are read as contiguous
-// runs and a wave covers 64 / L neighbouring rows per step; L follows the mean row length.
-// Workgroups take blocks of rows round-robin, which spreads heavy rows of a skewed degree
-// distribution over the grid.
 enum SweepOp { kCut = 0, kGapSum = 1, kBandwidth = 2 };
 
-template <typename RowT, typename AttrT, int L, int OP>
-__global__ __launch_bounds__(kBlock) void csr_sweep_kernel(int64_t n, int64_t nnz, int32_t k,
-                                                            const RowT *__restrict__ rowptr,
-                                                            const int32_t *__restrict__ colidx,
-                                                            const AttrT *__restrict__ attr,
-                                                            unsigned long long *__restrict__ out) {
-    __shared__ uint64_t red[kBlock / 64];
-    constexpr int kRowsPerBlock = kBlock / L;
-    const int sub = threadIdx.x % L;
-    const int64_t row_in_block = threadIdx.x / L;
-    const int64_t blocks_of_rows = (n + kRowsPerBlock - 1) / kRowsPerBlock;
-    uint64_t acc = 0;        // per-lane sum (gap, bandwidth)
-    uint32_t wave_cut = 0;   // per-wave count (cut), identical in every lane
-    for (int64_t rb = blockIdx.x; rb < blocks_of_rows; rb += gridDim.x) {
-        const int64_t u = rb * kRowsPerBlock + row_in_block;
-        int64_t b = 0, e = 0, au = 0;
-        bool u_ok = false;
-        if (u < n) {
-            b = max((int64_t)rowptr[u], (int64_t)0);
-            e = min((int64_t)rowptr[u + 1], nnz);
-            au = attr ? (int64_t)attr[u] : u;
-            if (OP == kCut) u_ok = sizeof(AttrT) == 1 ? au != 255 : (au >= 0 && au < k);
-        }
-        uint64_t widest = 0;
-        // All lanes of the wave run the same number of steps (until the longest row of the wave is
-        // done), so the ballot that counts cut entries is taken with every lane present.
-        const int64_t len = e - b;
-        for (int64_t t = sub; __ballot(t < len) != 0; t += L) {
-            const int64_t p = b + t;
-            bool hit = false;
-            if (p < e) {
-                const int32_t v = colidx[p];
-                if (v >= 0 && v < n) {
-                    const int64_t av = attr ? (int64_t)attr[v] : (int64_t)v;
-                    if (OP == kCut) {
-                        const bool v_ok = sizeof(AttrT) == 1 ? av != 255 : (av >= 0 && av < k);
-                        hit = u_ok && v_ok && au != av;
-                    } else {
-                        const uint64_t gap = (uint64_t)(au > av ? au - av : av - au);
-                        if (OP == kGapSum) acc += gap; else widest = gap > widest ? gap : widest;
-                    }
-                }
-            }
-            if (OP == kCut) wave_cut += (uint32_t)__popcll(__ballot(hit));
-        }
-        if (OP == kBandwidth) {
-            for (int off = L / 2; off > 0; off >>= 1) {
-                const uint64_t o = __shfl_xor(widest, off, 64);
-                widest = o > widest ? o : widest;
-            }
-            if (sub == 0) acc += widest;
-        }
-    }
-    if (OP == kCut) acc = (threadIdx.x & 63) == 0 ? wave_cut : 0;
-    const uint64_t total = block_sum_u64(acc, red);
-    if (threadIdx.x == 0 && total) atomicAdd(out, (unsigned long long)total);
-}
-
-// Edge-parallel sweep for sums over entries (cut count, gap sum).  A wave takes 64 consecutive
+// Edge-parallel sweep (cut count, gap sum, bandwidth sum).  A wave takes 64 consecutive
 // rows: their offsets (one coalesced load) and their attributes go to a wave-private LDS window,
 // and the rows' entries, which are one contiguous run of colidx, are streamed 256 at a time with
 // 16-byte loads, the next step's loads in flight while the current one is worked on.  A lane finds
 // the row of its first entry by bisecting the 64 row ends in LDS and walks forward from there,
-// so row length (empty rows, hubs) does not change the access pattern.
+// so row length (empty rows, hubs) does not change the access pattern.  Bandwidth: the widest gap of every row of the
+// window is kept in LDS (a lane folds the run of entries it has of a row before it looks there).
+// Bandwidth without ids, 122 M entries: 181 us = 2.8 TB/s; with a group of lanes per row (offsets, columns and a
+// reduction waited for row by row) 581 us.  At 280,000 entries 17 against 26 us.
 template <typename RowT, typename AttrT, int OP>
 __global__ __launch_bounds__(kBlock) void edge_block_sweep_kernel(int64_t n, int64_t nnz, int32_t k,
                                                                    const RowT *__restrict__ rowptr,
@@ -179,11 +120,16 @@ __global__ __launch_bounds__(kBlock) void edge_block_sweep_kernel(int64_t n, int
     constexpr int kWavesPerBlock = kBlock / 64;
     __shared__ int64_t rp_lds[kWavesPerBlock][66];
     __shared__ int32_t au_lds[kWavesPerBlock][64];
+    __shared__ uint32_t widest_lds[OP == kBandwidth ? kWavesPerBlock : 1][64];
     __shared__ uint64_t red[kWavesPerBlock];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int64_t *rp = rp_lds[wave];
     int32_t *aus = au_lds[wave];
+    uint32_t *widest = widest_lds[OP == kBandwidth ? wave : 0];
+    auto note_widest = [&](int j, uint32_t gap) {
+        if (widest[j] < gap) atomicMax(&widest[j], gap);
+    };
     const int64_t row_blocks = (n + 63) / 64;
     uint64_t acc = 0;
     uint32_t wave_cut = 0;
@@ -201,6 +147,7 @@ __global__ __launch_bounds__(kBlock) void edge_block_sweep_kernel(int64_t n, int
             int32_t a = 0;
             if (r0 + lane < n) a = attr ? (int32_t)attr[r0 + lane] : (int32_t)(r0 + lane);
             aus[lane] = a;
+            if (OP == kBandwidth) widest[lane] = 0;
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -251,12 +198,16 @@ __global__ __launch_bounds__(kBlock) void edge_block_sweep_kernel(int64_t n, int
             }
             int64_t row_end = rp[min(j + 1, 64)];
             int64_t au = aus[min(j, 63)];
-            uint32_t hits = 0;
+            uint32_t hits = 0, run = 0;   // run: the widest gap among this lane's entries of row j
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const int64_t pe = p + t;
                 const bool live = pe >= e_begin && pe < e_end;
                 if (live) {
+                    if (OP == kBandwidth && pe >= row_end) {
+                        note_widest(j, run);
+                        run = 0;
+                    }
                     while (pe >= row_end) {  // ends: pe < e_end = rp[64]
                         ++j;
                         row_end = rp[j + 1];
@@ -270,17 +221,23 @@ __global__ __launch_bounds__(kBlock) void edge_block_sweep_kernel(int64_t n, int
                                                                : (au >= 0 && au < k && av >= 0 && av < k);
                             hits += (ok && au != av) ? 1u : 0u;
                         } else {
-                            acc += (uint64_t)(au > av ? au - av : av - au);
+                            const uint64_t gap = (uint64_t)(au > av ? au - av : av - au);
+                            if (OP == kGapSum) acc += gap;
+                            else run = max(run, (uint32_t)gap);   // 32-bit ids: below 2^32
                         }
                     }
                 }
             }
+            if (OP == kBandwidth) note_widest(min(j, 63), run);
             if (OP == kCut) wave_cut += hits;
             cur = nxt;
             gcur = gnxt;
             nxt = nn;
         }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (OP == kBandwidth) acc += widest[lane];
     }
     if (OP == kCut) acc = wave_cut;
     const uint64_t total = block_sum_u64(acc, red);
@@ -297,36 +254,11 @@ int launch_edge_blocks(int64_t n, int64_t nnz, int32_t k, const RowT *rowptr, co
     return EP_OK;
 }
 
-template <typename RowT, typename AttrT, int OP>
-int launch_sweep(int64_t n, int64_t nnz, int32_t k, const RowT *rowptr, const int32_t *colidx, const AttrT *attr,
-                 unsigned long long *out, hipStream_t s) {
-    const double mean = (double)nnz / (double)n;
-    const int lanes = mean <= 6 ? 4 : mean <= 12 ? 8 : mean <= 24 ? 16 : mean <= 48 ? 32 : 64;
-    const int64_t blocks_of_rows = ceil_div(n, kBlock / lanes);
-    const unsigned grid = (unsigned)std::min<int64_t>(blocks_of_rows, 256 * 16);
-#define EP_SWEEP(L_) csr_sweep_kernel<RowT, AttrT, L_, OP><<<grid, kBlock, 0, s>>>(n, nnz, k, rowptr, colidx, attr, out)
-    switch (lanes) {
-        case 4: EP_SWEEP(4); break;
-        case 8: EP_SWEEP(8); break;
-        case 16: EP_SWEEP(16); break;
-        case 32: EP_SWEEP(32); break;
-        default: EP_SWEEP(64); break;
-    }
-#undef EP_SWEEP
-    EP_LAUNCH_CHECK();
-    return EP_OK;
-}
-
 template <typename AttrT, int OP>
 int launch_sweep_rows(int64_t n, int64_t nnz, int32_t k, const void *rowptr, bool i64, const int32_t *colidx,
                       const AttrT *attr, unsigned long long *out, hipStream_t s) {
-    if (OP != kBandwidth)
-        return i64 ? launch_edge_blocks<int64_t, AttrT, OP>(n, nnz, k, static_cast<const int64_t *>(rowptr), colidx,
-                                                            attr, out, s)
-                   : launch_edge_blocks<int32_t, AttrT, OP>(n, nnz, k, static_cast<const int32_t *>(rowptr), colidx,
-                                                            attr, out, s);
-    return i64 ? launch_sweep<int64_t, AttrT, OP>(n, nnz, k, static_cast<const int64_t *>(rowptr), colidx, attr, out, s)
-               : launch_sweep<int32_t, AttrT, OP>(n, nnz, k, static_cast<const int32_t *>(rowptr), colidx, attr, out, s);
+    return i64 ? launch_edge_blocks<int64_t, AttrT, OP>(n, nnz, k, static_cast<const int64_t *>(rowptr), colidx, attr, out, s)
+               : launch_edge_blocks<int32_t, AttrT, OP>(n, nnz, k, static_cast<const int32_t *>(rowptr), colidx, attr, out, s);
 }
 
 // ---- stable LSD radix sort of vertex ids by label, 8 bits per pass ----------------------

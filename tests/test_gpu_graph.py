@@ -65,6 +65,19 @@ def test_graph_with_empty_rows_hubs_and_ragged_sizes():
         _check_all(gr, _labels(n, 16_384, 4), 16_384)
 
 
+@pytest.mark.parametrize("n", [63, 64, 65, 129])
+@pytest.mark.parametrize("length", [1, 3, 4, 255, 256, 257, 1025])
+def test_sweeps_at_the_edges_of_windows_and_steps(n, length):
+    """Windows of 64 rows, steps of 256 entries, four entries per lane: rows of one length around those sizes, with
+    empty rows at both ends of a window, so that the entries of a lane belong to up to four rows."""
+    rng = np.random.default_rng(n + length)
+    deg = np.full(n, length)
+    deg[[0, n // 2, 62]] = 0
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    gr = Graph(torch.from_numpy(rowptr), torch.from_numpy(rng.integers(0, n, size=rowptr[-1]).astype(np.int32)))
+    _check_all(gr, _labels(n, 5, n), 5)
+
+
 def test_graph_without_edges_and_single_vertex():
     gr = Graph(torch.zeros(6, dtype=torch.int32), torch.zeros(0, dtype=torch.int32))
     cut, sizes = gr.quality(torch.tensor([0, 1, 1, 2, 2], dtype=torch.int32, device=DEV), 3)
