@@ -71,7 +71,7 @@ uint64_t splitmix64(uint64_t &state) {
 int do_assign(const ep_problem &p, const void *X, const float *C, const KmeansWs &w, int32_t *labels,
               float *min_d2, double *objective, hipStream_t s) {
     if (small_path_supported(p)) return launch_small_assign(p, X, C, w, labels, min_d2, objective, s);
-    if (small_sliced_supported(p)) return launch_small_assign_sliced(p, X, C, w, labels, min_d2, objective, s);
+    if (blocks_path_supported(p)) return launch_blocks_assign(p, X, C, w, labels, min_d2, objective, s);
     if (large_path_supported(p)) return launch_large_assign(p, X, C, w, labels, min_d2, objective, s);
     return launch_wide_assign(p, X, C, w, labels, min_d2, objective, s);
 }

@@ -70,7 +70,9 @@ struct KmeansWs {
     unsigned char *wide_records;  // wide kernels: centroids as matrix-instruction operands (shares its place with what the update uses)
     float *wide_bias;     // wide kernels: -||c_j||^2 / 2
     int64_t *idx;         // [k] init row indices
-    float *best_score;    // [n] best score over the centroid slices seen so far (fp32, d in {64,128}, k > 64)
+    unsigned char *block_records;   // fp32-accurate assignment of many clusters: centroids as matrix-instruction operands
+    int block_slice;                // records that block_records has room for
+    unsigned long long *winner;     // [n] (score, -index) of the best centroid so far (shares its place with order, order_tmp)
     int32_t *order;       // [n]  rows sorted by label           (large k)
     int32_t *order_tmp;   // [n]
     int64_t *seg;         // [k+1] segment offsets               (large k)
@@ -81,7 +83,8 @@ struct KmeansWs {
     int32_t *best_tile;   // [n] code of the 4 candidate centroid rows per point (large-k path)
     size_t bytes;
 };
-// records_over_sums: the wide kernels' records lie over the running sums, for callers that never chunk an update.
+// records_over_sums: for callers that never chunk an update.  The centroids' records take the place of the running sums
+// (which stay unused then), as far as there is room for them.
 KmeansWs carve_kmeans_ws(const ep_problem &p, void *ws, bool records_over_sums = false);
 
 int launch_gather_rows(const ep_problem &p, const void *X, const int64_t *idx_dev, float *C, hipStream_t s);
@@ -120,10 +123,6 @@ int launch_small_assign(const ep_problem &p, const void *X, const float *C, cons
                         float *min_d2, double *objective, hipStream_t s);
 int launch_small_update(const ep_problem &p, const void *X, const int32_t *labels, const float *C_prev,
                         float *C_out, int64_t *counts, const KmeansWs &w, const UpdateAcc &acc, hipStream_t s);
-// fp32, d in {64,128}, k > 64: the same assignment kernel over slices of 64 centroids (k / 64 passes).
-bool small_sliced_supported(const ep_problem &p);
-int launch_small_assign_sliced(const ep_problem &p, const void *X, const float *C, const KmeansWs &w, int32_t *labels,
-                               float *min_d2, double *objective, hipStream_t s);
 // One fused round: assign against C, sums, then C <- means (in place), *objective <- this
 // round's objective.
 // first_round: the data-only term of the objective (sum ||x||^2) is computed and kept in the
@@ -173,6 +172,12 @@ int launch_bounds_pass(const ep_problem &p, const int32_t *labels, const BoundsW
 // of the rows that changed label in kw.psum / kw.pcnt.
 int launch_bounds_round(const ep_problem &p, const void *X, const float *C, const KmeansWs &kw, const BoundsWs &w,
                         int32_t *labels, hipStream_t s);
+
+// ---- K-Means, k > 64, fp32 and fp16 rows of up to 128 columns (kmeans_blocks.hip) -------------------
+bool blocks_path_supported(const ep_problem &p);
+size_t block_record_bytes(const ep_problem &p);   // of one record (32 centroids)
+int launch_blocks_assign(const ep_problem &p, const void *X, const float *C, const KmeansWs &w, int32_t *labels,
+                         float *min_d2, double *objective, hipStream_t s);
 
 // ---- K-Means, k > 64, bf16, d in {64,128}: bf16 matrix-core assignment (kmeans_large.hip) -------
 bool large_path_supported(const ep_problem &p);

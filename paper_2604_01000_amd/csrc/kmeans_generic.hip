@@ -274,7 +274,8 @@ KmeansWs carve_kmeans_ws(const ep_problem &p, void *ws, bool records_over_sums) 
     KmeansWs w{};
     const size_t kd = (size_t)p.k * p.d;
     const bool small = small_path_supported(p), large = large_path_supported(p);
-    const bool wide = !small && !large && !small_sliced_supported(p);
+    const bool blocks = !small && blocks_path_supported(p);
+    const bool wide = !small && !large && !blocks;
     const size_t rec_bytes = wide ? wide_record_bytes(p) : 0;
     w.obj_part = c.take<double>(kObjBlocksMax);
     // the running sums of a chunked update come first: their place must not depend on n, because the
@@ -289,8 +290,7 @@ KmeansWs carve_kmeans_ws(const ep_problem &p, void *ws, bool records_over_sums) 
         w.records = c.take<unsigned char>(large_record_bytes(p));
         w.best_tile = c.take<int32_t>((size_t)p.n);
     }
-    if (wide) w.wide_bias = c.take<float>(wide_bias_elems(p));
-    if (small_sliced_supported(p)) w.best_score = c.take<float>((size_t)p.n);
+    if (wide && !update_by_sorted_rows(p)) w.wide_bias = c.take<float>(wide_bias_elems(p));
     if (small) {
         w.psum = c.take<float>((size_t)kUpdBlocksMax * (size_t)p.k * (size_t)small_padded_d(p));
         w.pcnt = c.take<int32_t>((size_t)kUpdBlocksMax * p.k);
@@ -300,6 +300,31 @@ KmeansWs carve_kmeans_ws(const ep_problem &p, void *ws, bool records_over_sums) 
         w.psum = reinterpret_cast<float *>(both);
         w.wide_records = both;
         w.pcnt = c.take<int32_t>(wide_pcnt_elems(p));
+    } else if (blocks) {
+        // the winners lie over the row order, the records over what else only the update uses; with records_over_sums
+        // they take the larger of that and the running sums, as many at a time as fit there
+        const size_t n4 = align_up((size_t)p.n * 4, 256);
+        unsigned char *both = c.take<unsigned char>(2 * n4);
+        w.order = reinterpret_cast<int32_t *>(both);
+        w.order_tmp = reinterpret_cast<int32_t *>(both + n4);
+        w.winner = reinterpret_cast<unsigned long long *>(both);
+        const size_t start = align_up(c.used, 256), record = block_record_bytes(p);
+        const int64_t records = ceil_div(p.k, 32);
+        w.seg = c.take<int64_t>((size_t)p.k + 1);
+        w.sort_hist = c.take<int32_t>(sort_hist_elems());
+        const SegPlan sp = seg_plan(p, align_up(c.used, 256) + 256);
+        w.seg_pieces = sp.pieces;
+        if (sp.pieces > 1) w.seg_part = c.take<double>((size_t)p.k * sp.pieces * sp.part_elems());
+        if (!records_over_sums) c.used = std::max(c.used, start + (size_t)records * record);
+        size_t room = c.used - start;   // at least the radix sort's megabyte: dozens of records
+        w.block_records = reinterpret_cast<unsigned char *>(c.base ? c.base + start : nullptr);
+        if (records_over_sums && kd * 8 > room) {
+            room = kd * 8;
+            w.block_records = reinterpret_cast<unsigned char *>(w.acc_sum);
+        }
+        w.block_slice = (int)std::min<int64_t>(records, (int64_t)(room / record));
+        w.bytes = align_up(c.used, 256);
+        return w;
     } else {
         const size_t n4 = align_up((size_t)p.n * 4, 256);
         unsigned char *both = c.take<unsigned char>(std::max(2 * n4, records_over_sums ? 0 : rec_bytes));
@@ -308,6 +333,7 @@ KmeansWs carve_kmeans_ws(const ep_problem &p, void *ws, bool records_over_sums) 
         w.wide_records = both;
         w.seg = c.take<int64_t>((size_t)p.k + 1);
         w.sort_hist = c.take<int32_t>(sort_hist_elems());
+        if (wide) w.wide_bias = reinterpret_cast<float *>(w.sort_hist);   // (the assignment's)
         // (the parts must not depend on where the records lie: count them as lying over the sums)
         const size_t moved = records_over_sums ? 0 : align_up(std::max(kd * 8, rec_bytes), 256) - align_up(kd * 8, 256);
         const size_t shared = records_over_sums ? 0 : align_up(std::max(2 * n4, rec_bytes), 256) - 2 * n4;

@@ -94,30 +94,6 @@ __global__ __launch_bounds__(256) void wide_prep_kernel(int32_t d, int32_t k, in
 }
 
 // ---- 2. assignment ----------------------------------------------------------------------------------
-constexpr float kNoScore = -3.4e38f;   // no score was ordered above it: a row with an infinity or a NaN
-
-// The scores of a row in plain fp32, for the rows whose split has no value (the terms of an infinity are infinity
-// and NaN).  A row with an infinity takes the first centroid whose product with it is +infinity; one with a NaN keeps
-// label 0, as comparisons with NaN leave it.
-template <typename XT>
-__device__ void plain_scores(const XT *x, int32_t d, const float *C, const float *bias, int32_t k, float &best, int32_t &idx) {
-    bool nan = false;
-    for (int m = 0; m < d; ++m) {
-        const float v = load_elem(x + m);
-        nan |= v != v;
-    }
-    if (nan) return;
-    for (int32_t j = 0; j < k; ++j) {
-        float s = bias[j];
-        for (int m = 0; m < d; ++m) {
-            float c = C[(int64_t)j * d + m];
-            if (std::is_same<XT, bf16_t>::value) c = bf16_to_f32(f32_to_bf16_rne(c));
-            s = fmaf(load_elem(x + m), c, s);
-        }
-        if (s > best) { best = s; idx = j; }
-    }
-}
-
 // XN: also ||x||^2 (min_d2 or the objective is wanted).
 template <typename XT, int KT, int PT, bool XN>
 __global__ __launch_bounds__(kAssignThreads, 2) void wide_assign_kernel(
@@ -283,7 +259,7 @@ __global__ __launch_bounds__(kAssignThreads, 2) void wide_assign_kernel(
         }
         const int64_t i = tile * tile_rows + (wave * PT + g) * 16 + c;
         if (__builtin_expect(__any(g < PT && i < n && my_best == kNoScore), 0))
-            if (g < PT && i < n && my_best == kNoScore) plain_scores(X + i * ld, d, C, bias, k, my_best, my_idx);
+            if (g < PT && i < n && my_best == kNoScore) plain_scores(X + i * ld, d, C, k, my_best, my_idx, [&](int32_t j) { return bias[j]; });
         if (g < PT && i < n) {
             labels[i] = my_idx;
             if (XN) {

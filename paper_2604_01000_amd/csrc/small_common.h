@@ -3,6 +3,8 @@
 // three-way bf16 split, the bf16 matrix-instruction wrappers and the rank-ordered row adds into LDS sums.
 #pragma once
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace ep {
@@ -72,6 +74,30 @@ __device__ __forceinline__ f32x4 mfma_bf16_k16(const u32x2 &a, const u32x2 &b, c
 __device__ __forceinline__ f32x4 mfma_bf16_k32(const u32x4 &a, const u32x4 &b, const f32x4 &acc) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
                                                    acc, 0, 0, 0);
+}
+
+constexpr float kNoScore = -3.4e38f;   // no score was ordered above it: a row with an infinity or a NaN
+
+// The scores of a row in plain fp32, for the rows whose split has no value (the terms of an infinity are infinity
+// and NaN).  A row with an infinity takes the first centroid whose product with it is +infinity; one with a NaN keeps
+// label 0, as comparisons with NaN leave it.  bias(j) = -||c_j||^2 / 2.
+template <typename XT, typename Bias>
+__device__ void plain_scores(const XT *x, int32_t d, const float *C, int32_t k, float &best, int32_t &idx, const Bias &bias) {
+    bool nan = false;
+    for (int m = 0; m < d; ++m) {
+        const float v = load_elem(x + m);
+        nan |= v != v;
+    }
+    if (nan) return;
+    for (int32_t j = 0; j < k; ++j) {
+        float s = bias(j);
+        for (int m = 0; m < d; ++m) {
+            float c = C[(int64_t)j * d + m];
+            if (std::is_same<XT, bf16_t>::value) c = bf16_to_f32(f32_to_bf16_rne(c));
+            s = fmaf(load_elem(x + m), c, s);
+        }
+        if (s > best) { best = s; idx = j; }
+    }
 }
 
 // Distance bounds of the bounded rounds, kept on the safe side of fp32 rounding: an upper bound is rounded up, a

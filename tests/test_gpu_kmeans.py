@@ -74,10 +74,10 @@ SHAPES = [  # n, d, k, relu, dtype, ld
     (3001, 256, 16, False, torch.float32, 260),
     (2999, 256, 7, True, torch.bfloat16, None),
     (3000, 256, 20, True, torch.float32, None),      # d = 256, k > 16: generic kernels
-    (6000, 128, 100, True, torch.float32, None),     # fp32 with k > 64: assignment in slices of 64 centroids,
-    (4097, 128, 65, True, torch.float32, 132),       # one full slice and a slice of one centroid,
-    (3000, 64, 129, False, torch.float32, None),     # two full slices and one more centroid,
-    (5001, 128, 1000, True, torch.float32, None),    # 16 slices; update: segments cut in parts
+    (6000, 128, 100, True, torch.float32, None),     # fp32 with k > 64: records of 32 centroids,
+    (4097, 128, 65, True, torch.float32, 132),       # a last record of one centroid,
+    (3000, 64, 129, False, torch.float32, None),     # four full records and one more centroid,
+    (5001, 128, 1000, True, torch.float32, None),    # update: segments cut in parts
     (5000, 64, 200, False, torch.float32, 68),
     (4001, 100, 12, True, torch.float32, None),      # d not a template size: columns padded with zeros on the fly
     (3001, 36, 40, True, torch.float32, 40),         # (d = 36 in the 64-column kernel, four centroid tiles)
@@ -88,7 +88,7 @@ SHAPES = [  # n, d, k, relu, dtype, ld
     (7777, 128, 16, True, torch.float16, 136),
     (3001, 64, 30, False, torch.float16, None),
     (3001, 20, 5, False, torch.float16, 24),         # (generic kernels)
-    (6000, 128, 100, True, torch.float16, None),     # (k > 64: slices of 64 centroids, update by sorted rows)
+    (6000, 128, 100, True, torch.float16, None),     # (k > 64: update by sorted rows)
     (2999, 200, 9, True, torch.float16, None),       # (columns padded on the fly)
     (64, 128, 64, False, torch.float32, None),      # k == n
     (1, 64, 1, False, torch.float32, None),
@@ -120,7 +120,7 @@ def test_assign_ties_take_the_lowest_index():
 
 
 def test_assign_ties_across_centroid_slices():
-    """fp32 with k > 64 is assigned in slices of 64 centroids: a duplicate in a later slice must not take
+    """k > 64: a duplicate in a later record of centroids, swept by another workgroup, must not take
     the point from the earlier one, and the returned distances and objective are those of the winner."""
     X = _mixture(4000, 128, 6, seed=8)
     X32 = to_np32(X)
