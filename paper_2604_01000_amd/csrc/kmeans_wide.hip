@@ -24,9 +24,10 @@
 //  4. wide_finalize_kernel: fp64 sum of the partials in a fixed order, means.
 //
 // What bounds them: memory, twice over X per round (the sums need the labels of whole rows).  Measured per round at
-// 500,003 x 256 fp32, k = 32: assignment 101 us = 5.1 TB/s, sums 88 us = 5.8 TB/s; before (one point per lane on the
-// vector unit, then a table of sums in LDS, then one thread adding 1,024 partials) 474 + 465 + 258 us, and a single
-// thread adding the objective 117 us.  200,003 x 516 bf16, k = 20: 45 + 44 us against 353 us + 62 ms (one wave per
+// 500,003 x 256 fp32, k = 32: assignment 99 us = 5.2 TB/s, sums 86 us = 6.0 TB/s (104 and 91 us with one K-step in flight
+// and parts of consecutive rows); on the vector unit (one point per lane, then a table of sums in LDS, then one thread
+// adding 1,024 partials) 474 + 465 + 258 us, and a single thread adding the objective 117 us.  200,003 x 516 bf16,
+// k = 20: 47 + 41 us (the sums 46 us with two waves more than are resident at once) against 353 us + 62 ms (one wave per
 // cluster walked its rows).
 #include <algorithm>
 #include <atomic>
@@ -127,16 +128,27 @@ __global__ __launch_bounds__(kAssignThreads, 2) void wide_assign_kernel(
             row[p] = X + (i < n ? i : n - 1) * ld;
         }
     };
-    // Raw pieces of K-step ks.  A piece that starts past the last column is read from column 0 instead and masked
+    // Raw pieces of a K-step.  A piece that starts past the last column is read from column 0 instead and masked
     // where it is used; one that holds any column ends inside the row (the stride is a multiple of a piece).
-    auto load_step = [&](int ks, u32x4(&dst)[PT][NP]) {
+    int lks = 0, lcb = 0;   // the step that is loaded next, ahead of the one worked on, in the next tile if need be
+    int64_t ltile = blockIdx.x;
+    auto load_next = [&](u32x4(&dst)[PT][NP]) {
+        if (lks == ksteps) {
+            lks = 0;
+            if (++lcb == blocks_of_centroids) {
+                lcb = 0;
+                ltile += gridDim.x;
+                point_at(ltile);
+            }
+        }
 #pragma unroll
         for (int q = 0; q < NP; ++q) {
-            const int col = ks * kStep + 4 * PE * q + PE * g;
+            const int col = lks * kStep + 4 * PE * q + PE * g;
             const int at = col < d ? col : 0;
 #pragma unroll
             for (int p = 0; p < PT; ++p) dst[p][q] = *reinterpret_cast<const u32x4 *>(row[p] + at);
         }
+        ++lks;
     };
 
     float best[PT], xn[PT];
@@ -144,7 +156,7 @@ __global__ __launch_bounds__(kAssignThreads, 2) void wide_assign_kernel(
     f32x4 acc[PT][KT];
     int ks = 0, cb = 0;
 
-    auto step = [&](u32x4(&x)[PT][NP], u32x4(&nxt)[PT][NP], int64_t tile) {
+    auto step = [&](u32x4(&x)[PT][NP], u32x4(&ahead)[PT][NP]) {
         if (ks % panel_steps == 0 && !staged) {   // uniform over the workgroup
             __syncthreads();
             const int steps = min(panel_steps, ksteps - ks);
@@ -162,8 +174,7 @@ __global__ __launch_bounds__(kAssignThreads, 2) void wide_assign_kernel(
             }
         }
         const bool last_step = ks + 1 == ksteps;
-        if (last_step && cb + 1 == blocks_of_centroids) point_at(tile + gridDim.x);   // the next tile's first step comes next
-        load_step(last_step ? 0 : ks + 1, nxt);
+        load_next(ahead);
 
         // this step's operand: the rows' terms (columns past d become zeros: they may hold anything in memory)
         u32x4 xt[TX][PT];
@@ -274,13 +285,16 @@ __global__ __launch_bounds__(kAssignThreads, 2) void wide_assign_kernel(
         for (int p = 0; p < PT; ++p) best[p] = kNoScore, bidx[p] = 0, xn[p] = 0.f;
         cb = 0;
     };
-    // One K-step is worked on while the next one (of the next tile, if need be) is in flight.
-    u32x4 xa[PT][NP], xb[PT][NP];
+    // One K-step is worked on while the next two are in flight (fp32 rows and four centroid tiles: the next one, there
+    // are no registers for more).
+    constexpr bool kTwoAhead = !(kF32 && KT == 4 && PT == 4);
+    u32x4 xa[PT][NP], xb[PT][NP], xc[PT][NP];
     int64_t tile = blockIdx.x;
     bool more = tile < tiles;   // uniform over the workgroup
     if (more) {
         point_at(tile);
-        load_step(0, xa);
+        load_next(xa);
+        if (kTwoAhead) load_next(xb);
         begin_tile();
     }
     auto advance = [&]() {
@@ -291,11 +305,16 @@ __global__ __launch_bounds__(kAssignThreads, 2) void wide_assign_kernel(
         begin_tile();
     };
     while (more) {
-        step(xa, xb, tile);
+        step(xa, kTwoAhead ? xc : xb);
         advance();
         if (!more) break;
-        step(xb, xa, tile);
+        step(xb, xa);
         advance();
+        if (kTwoAhead) {
+            if (!more) break;
+            step(xc, xb);
+            advance();
+        }
     }
     if (XN && obj_part) {
         for (int off = 32; off > 0; off >>= 1) obj += __shfl_down(obj, off, 64);
@@ -319,7 +338,7 @@ __global__ __launch_bounds__(64) void wide_objective_kernel(const double *__rest
 }
 
 // ---- 3. sums for k <= 64 ------------------------------------------------------------------------------
-// A wave owns a slab of 16 NC columns and a contiguous range of 32-row groups ("part"); it leaves the sums of
+// A wave owns a slab of 16 NC columns and every parts-th 32-row group ("part"); it leaves the sums of
 // its rows in psum[part][k][dpad] (dpad = slabs * 16 NC) and, on slab 0, their counts in pcnt[part][k].
 template <typename XT> constexpr int slab_cols() { return 16 * (16 / (int)sizeof(XT)); }
 int slab_cols_of(int dtype) { return dtype == EP_F32 ? slab_cols<float>() : slab_cols<bf16_t>(); }
@@ -328,9 +347,8 @@ int64_t slabs_of(const ep_problem &p) { return ceil_div(p.d, slab_cols_of(p.dtyp
 typedef int i32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 template <typename XT, int KT>
-__global__ __launch_bounds__(256, 2) void wide_sums_kernel(int64_t n, int32_t d, int32_t k, int64_t ld, int32_t slabs,
-                                                           int32_t parts, int64_t groups_per_part,
-                                                           int64_t parts_with_one_more, const XT *__restrict__ X,
+__global__ __launch_bounds__(256, KT == 4 && sizeof(XT) == 2 ? 1 : 2) void wide_sums_kernel(int64_t n, int32_t d, int32_t k, int64_t ld, int32_t slabs,
+                                                           int32_t parts, int64_t groups, const XT *__restrict__ X,
                                                            const int32_t *__restrict__ labels, float *__restrict__ psum,
                                                            int32_t *__restrict__ pcnt) {
     constexpr bool kF32 = std::is_same<XT, float>::value, kBf16 = std::is_same<XT, bf16_t>::value;
@@ -340,8 +358,9 @@ __global__ __launch_bounds__(256, 2) void wide_sums_kernel(int64_t n, int32_t d,
     const int slab = (int)(unit % slabs);
     const int64_t part = unit / slabs;
     const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
-    const int64_t first = part * groups_per_part + min(part, parts_with_one_more);
-    const int64_t last = first + groups_per_part + (part < parts_with_one_more ? 1 : 0);
+    // the groups part, part + parts, ..., the last one first: the assignment has just read the end of X, and what the
+    // memory-side cache still holds of it is read again before it is lost
+    int64_t grp = part + (groups - 1 - part) / parts * parts;   // (part < parts <= groups)
     const int col = slab * 16 * NC + NC * c;
     const XT *Xc = X + (col < d ? col : 0);   // a lane without columns reads column 0; its sums are never used
 
@@ -424,17 +443,17 @@ __global__ __launch_bounds__(256, 2) void wide_sums_kernel(int64_t n, int32_t d,
     };
     u32x4 xa[8], xb[8];
     i32x4 la[2], lb[2];
-    int64_t grp = first;
-    if (grp < last) load_rows(grp, xa, la);
-    while (grp < last) {
-        load_rows(grp + 1 < last ? grp + 1 : grp, xb, lb);
+    load_rows(grp, xa, la);
+    while (grp >= 0) {
+        load_rows(grp >= parts ? grp - parts : grp, xb, lb);
         __builtin_amdgcn_sched_barrier(0);
         add(xa, la);
-        if (++grp >= last) break;
-        load_rows(grp + 1 < last ? grp + 1 : grp, xa, la);
+        grp -= parts;
+        if (grp < 0) break;
+        load_rows(grp >= parts ? grp - parts : grp, xa, la);
         __builtin_amdgcn_sched_barrier(0);
         add(xb, lb);
-        ++grp;
+        grp -= parts;
     }
     // An infinity or a NaN times the zeros of the one-hot operand is a NaN in every centroid's sum: then this part's
     // rows are added again one by one, each to its own centroid only.  (Columns past d may hold anything.)
@@ -452,7 +471,8 @@ __global__ __launch_bounds__(256, 2) void wide_sums_kernel(int64_t n, int32_t d,
         for (int mt = 0; mt < KT; ++mt)
 #pragma unroll
             for (int t = 0; t < NC; ++t) acc[mt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int64_t r = first * 32; r < min(n, last * 32); ++r) {
+        for (int64_t q = 0; part * 32 + (q >> 5) * 32 * parts + (q & 31) < n; ++q) {
+            const int64_t r = part * 32 + (q >> 5) * 32 * parts + (q & 31);
             const int32_t l = labels[r];
             const u32x4 x = *reinterpret_cast<const u32x4 *>(Xc + r * ld);
 #pragma unroll
@@ -562,12 +582,12 @@ int by_cent_tiles(int kt, F &&f) {
     }
 }
 
-// Row parts of the sums: enough waves to fill the chip eight deep, at least two 32-row groups each, and no more
-// partials than the workspace holds.
+// Row parts of the sums: as many waves as are resident at once (8 per compute unit; two more than that took 46 instead
+// of 41 us at 200,003 x 516 bf16), at least two 32-row groups each, and no more partials than the workspace holds.
 int wide_parts(const ep_problem &p) {
     const int64_t groups = ceil_div(p.n, 32), slabs = slabs_of(p);
     const int64_t dpad = slabs * slab_cols_of(p.dtype);
-    int64_t parts = std::min<int64_t>(ceil_div(256 * 8, slabs), ceil_div(groups, 2));
+    int64_t parts = std::min<int64_t>(256 * 8 / slabs, ceil_div(groups, 2));
     parts = std::min<int64_t>(parts, kWidePartialElems / (p.k * dpad));
     return (int)std::max<int64_t>(1, parts);
 }
@@ -644,7 +664,7 @@ int launch_wide_update(const ep_problem &p, const void *X, const int32_t *labels
         return by_cent_tiles(cent_tiles(p.k), [&](auto kt_) {
             ProfScope prof(EP_PROF_UPDATE_SUMS, s);
             wide_sums_kernel<XT, decltype(kt_)::value><<<(unsigned)ceil_div((int64_t)slabs * parts, 4), 256, 0, s>>>(
-                p.n, p.d, p.k, p.ld, slabs, parts, groups / parts, groups % parts, static_cast<const XT *>(X), labels, w.psum,
+                p.n, p.d, p.k, p.ld, slabs, parts, groups, static_cast<const XT *>(X), labels, w.psum,
                 w.pcnt);
             EP_LAUNCH_CHECK();
             return (int)EP_OK;
