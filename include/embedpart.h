@@ -303,7 +303,7 @@ int edge_gap_sum(int64_t n, int64_t nnz, const void *rowptr, int rowptr_is_i64,
  * to its free capacity: r = mix64(seed, round, v) mod F over the running sum of the free
  * capacities in partition order (mix64 = the splitmix64 output function applied to
  * seed + (round * 2^32 + v + 1) * 0x9E3779B97F4A7C15).  All draws of a round use the loads at its
- * start.  At most max_rounds rounds are enqueued; rounds after the last needed one do nothing.
+ * start.  At most max_rounds rounds run; the call ends with the last needed one.
  *   rowptr     n + 1 offsets, int32 or int64 (rowptr_is_i64); only the row lengths are used
  *   vclass     n bytes, class of every vertex, or NULL: all vertices form the class
  *   class_id   the class to balance (0..255)

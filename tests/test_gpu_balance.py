@@ -34,7 +34,7 @@ def _skewed_labels(n, k, seed):
 @pytest.mark.parametrize("n,k,beta,rounds,i64", [
     (1, 1, 1.0, 4, False), (257, 2, 1.0, 8, False), (5_003, 8, 1.05, 16, False), (20_011, 64, 1.2, 16, True),
     (70_001, 255, 1.05, 32, True), (40_000, 5, 1.0, 1, False), (40_000, 5, 1.0, 0, False),
-    # beyond 2^18 vertices the rounds run as a chain of launches instead of one
+    # many workgroups
     (300_007, 16, 1.05, 16, True), (280_001, 6, 1.1, 8, False), (262_144, 40, 1.05, 16, False), (262_145, 40, 1.05, 16, False),
 ])
 def test_balance_equals_oracle(n, k, beta, rounds, i64):
@@ -54,9 +54,8 @@ def test_balance_equals_oracle(n, k, beta, rounds, i64):
                                       (6_000, 3, 100_000, 2_000_000), (270_000, 8, 250, 3_000), (300_000, 200, 60, 400),
                                       (270_001, 3, 100_000, 2_000_000), (263_000, 64, 0, 16_000_000)])
 def test_balance_with_large_degrees_equals_oracle(n, k, lo, hi):
-    """Degrees beyond the exact bins of the degree histogram (min(256, 16384 / k) - 1 and up share the last bin):
-    the range that holds the threshold degree is counted again with narrower bins, inside the one launch of the
-    small graphs and as further launches of the chain beyond 2^18 vertices, until it is one degree wide.  All must
+    """Degrees beyond the exact bins of the degree histogram (min(256, 8192 / k) - 1 and up share the last bin):
+    the range that holds the threshold degree is counted again with narrower bins until it is one degree wide.  All must
     pick the oracle's movers.  (Degrees stay below 2^24, beyond which the device treats them as equal.)"""
     rng = np.random.default_rng(n + k)
     deg = rng.integers(lo, hi, n).astype(np.int64)
@@ -193,3 +192,27 @@ def test_calls_on_several_streams_do_not_disturb_each_other():
     torch.cuda.synchronize()
     for a, b in zip(got, want):
         np.testing.assert_array_equal(a.cpu().numpy(), b)
+
+
+@pytest.mark.parametrize("n", [30_000, 120_000, 300_000])
+def test_a_captured_call_replays_to_the_same_labels(n):
+    k = 12
+    rng = np.random.default_rng(n)
+    rowptr = torch.from_numpy(np.concatenate([[0], np.cumsum(rng.integers(0, 40, n))]).astype(np.int64)).to(DEV)
+    first = _skewed_labels(n, k, 1)
+    _device_balance(rowptr, first, k, 1.05, 5, 16)          # loads the kernels
+    start = torch.from_numpy(first).to(DEV)
+    lab, stats = start.clone(), torch.zeros(3, dtype=torch.int64, device=DEV)
+    ws = ep.workspace(ep.balance_workspace_bytes(n), DEV)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ep.partition_balance(n, k, rowptr, None, 0, 1.05, 5, 16, lab, stats, ws)
+    for seed in (1, 2, 3):
+        labels = _skewed_labels(n, k, seed)
+        want, want_stats = _device_balance(rowptr, labels, k, 1.05, 5, 16)
+        lab.copy_(torch.from_numpy(labels))
+        graph.replay()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(lab.cpu().numpy(), want)
+        np.testing.assert_array_equal(stats.cpu().numpy(), want_stats)
